@@ -258,6 +258,9 @@ struct MechGrid {
   DevGrid g;
   const uint8_t *fixed;   // per node: bit c = DOF c fixed
 };
+// Rows of partials (kRedWidth doubles each) that the solve's reductions on this
+// mesh may write, in either precision.
+int64_t mech_part_rows(const DevGrid &g);
 hipError_t launch_mech_diag(const MechGrid &M, double *dinv[3], hipStream_t s);
 hipError_t launch_mech_rhs(const MechGrid &M, const double *theta, double *f[3], double *partials,
                            DevScalars *sc, double rtol, hipStream_t s);

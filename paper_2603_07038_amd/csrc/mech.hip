@@ -381,6 +381,14 @@ inline int flat_blocks(int64_t n) { return int(std::max<int64_t>(1, std::min<int
 
 }  // namespace
 
+// Node blocks; the rows of the flat and stencil kernels (at most 1024 and 1563);
+// and the blocks of the HEX8 operator, which on a long mesh of few planes can be
+// more than the node blocks (its tiles own 31 x 7 nodes, a node block is 64 x 4).
+int64_t mech_part_rows(const DevGrid &g) {
+  const dim3 nb = node_grid(g);
+  return std::max({int64_t(nb.x) * nb.y * nb.z, int64_t(2048), cell_blocks<float>(g), cell_blocks<double>(g)});
+}
+
 hipError_t launch_mech_diag(const MechGrid &M, double *dinv[3], hipStream_t s) {
   hipLaunchKernelGGL(mech_diag_kernel, node_grid(M.g), dim3(BX, BY), 0, s, M, dinv[0], dinv[1], dinv[2]);
   return hipGetLastError();

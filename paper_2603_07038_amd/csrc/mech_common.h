@@ -217,8 +217,10 @@ inline dim3 cell_grid(const DevGrid &g, int kchunk) {
 // Planes per block.  The resident blocks (4 per CU in FP32, 2 in FP64, by
 // registers and LDS) march in step, so a launch takes about (generations of
 // blocks) x (planes per block + 2: the layer below the chunk and the start).
-// The number of chunks that makes this smallest is taken; the reduction's
-// partials (one row per block) hold max(1024, node blocks) rows.  On
+// The number of chunks that makes this smallest is taken, within the rows that
+// the reduction's partials always hold (one per block: max(1024, node blocks));
+// a mesh whose tiles alone are more takes one chunk, and a plan gives its
+// partials a row for each (mech_part_rows).  On
 // 257x257x65 nodes in FP32 that is 22 planes: 57.6 us for the residual and
 // 99.5 us for the smoothing step, against 70.6 and 105.9 us at 5 planes; on
 // 161x153x49 nodes 7 planes, 21.2 and 25.5 us against 24.1 and 29.3 us at 4.

@@ -477,7 +477,9 @@ etm_status derive(etm_plan *p, const etm_source *src) {
   take(p->r_sc, sizeof(DevScalars));
   // the mechanical solve owns its partials, scalars and temperature copy, so
   // that it can run beside the march on another stream
-  take(p->r_partm, size_t(std::max<int64_t>(p->nblocks_node, 2048)) * kRedWidth * 8);
+  DevGrid extent{};
+  extent.nx = nx; extent.ny = ny; extent.nz = nz;
+  take(p->r_partm, size_t(mech_part_rows(extent)) * kRedWidth * 8);
   take(p->r_scm, sizeof(DevScalars));
   take(p->r_ctl, sizeof(DevScalars));
   take(p->r_gR, sizeof(DevScalars));

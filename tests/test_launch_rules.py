@@ -1,0 +1,43 @@
+"""The sizes that launches and workspaces are planned with, on the CPU: a small
+program linked with the library answers queries (launch_rules.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2603_07038_amd as etm
+from paper_2603_07038_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(not shutil.which(B.HIPCC) and not os.path.exists(B.HIPCC),
+                                reason="hipcc not available")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    etm.load()  # (built)
+    exe = str(tmp_path_factory.mktemp("rules") / "launch_rules")
+    r = subprocess.run([B.HIPCC] + [f for f in B.FLAGS if f != "-O3"] + ["-O1", "-x", "hip",
+                       os.path.join(HERE, "launch_rules.cpp"), "-x", "none", B.LIB, "-Wl,-rpath," + B.HERE, "-o", exe],
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def query(lines):
+        r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-2000:]
+        out = r.stdout.splitlines()
+        assert len(out) == len(lines) and not any(x.startswith("error") for x in out), r.stdout
+        return [[int(v) for v in x.split()] for x in out]
+    return query
+
+
+# Long meshes of few planes have more operator tiles (31 x 7 nodes) than blocks
+# of 64 x 4 nodes; the last two are ordinary ones.
+@pytest.mark.parametrize("precision", [etm.ETM_PREC_FP64, etm.ETM_PREC_MIXED])
+def test_solver_partials_hold_every_block(ask, precision):
+    shapes = [(32800, 7, 1), (63999, 3, 1), (100000, 7, 1), (65000, 7, 2), (7, 60000, 1), (64, 70, 30000), (31, 7, 1),
+              (256, 256, 64)]
+    for shape, (rows, fp32, fp64) in zip(shapes, ask(["partials %d %d %d %d" % (precision, *s) for s in shapes])):
+        assert rows >= max(fp32, fp64), (shape, rows, fp32, fp64)
