@@ -380,7 +380,7 @@ struct MgLevel {
                            // at node n is A[((q * 3 + r) * n_nodes + n) * 3 + (0..2)] (see stencil_idx)
   T *Dinv;                 // [6][n] inverse nodal diagonal block (xx, yy, zz, xy, yz, xz); dead rows zero
   uint8_t *dead;           // per node: bit c = DOF c outside the space (fixed, or no stiffness)
-  V3<T> xa, xb, b;         // smoother iterates, right-hand side (coarse levels)
+  V3<T> xa, xb, d, b;      // smoother iterates, Chebyshev direction, right-hand side (coarse levels)
   MgAxis ax[3];            // interpolation from level + 1 (unused on the coarsest level)
   int deg;                 // Chebyshev steps on this level (1..kMgDeg)
   double c1[kMgDeg], c2[kMgDeg];

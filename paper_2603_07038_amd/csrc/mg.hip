@@ -479,12 +479,16 @@ __device__ __forceinline__ void dinv_apply(const T D[6], const T r[3], T z[3]) {
   z[2] = D[5] * r[0] + D[4] * r[1] + D[2] * r[2];
 }
 
-// A Chebyshev step is x_{k+1} = x_k + c1 (x_k - x_{k-1}) + c2 Dinv (b - A x_k).
-// x_{k-1} lies where x_{k+1} goes (a node reads its own entry before it
-// writes), so no direction vector is stored beside the two iterates: 74
-// instead of 86 bytes per level-0 node and step in FP32.  Where the step
-// before started:
-enum { kFromNone = 0, kFromZero = 1, kFromOut = 2 };  // no such step (c1 = 0), x = 0, the output's entries
+// A Chebyshev step is x_{k+1} = x_k + d_{k+1}, d_{k+1} = c1 d_k + c2 Dinv (b - A x_k).
+// The direction d is a vector of its own where a later step needs it.  A step
+// from x = 0 has d = x, so of the four steps of a cycle at the usual degree of 2
+// only the first after the coarse correction stores a direction, and the one
+// that reads it, the last, writes its result over it: a node reads its own entry
+// before it writes.  (Formed again as x_k - x_{k-1}, d is rounded like x and not
+// like itself: errors of thirty mixed solves of packages 2 % larger in the mean.
+// It needs no store: us per CG iteration 1188 | 1267 mixed and 2226 | 2311 FP64
+// on 257x257x65 nodes, 431 | 452 and 733 | 764 on 161x153x49.)
+enum { kDirNone = 0, kDirX = 1, kDirKept = 2 };  // d_k: none (c1 = 0), x itself, stored
 
 // First Chebyshev step from x = 0 at node n (a node index or a NodeAt):
 // x = c2 Dinv b.
@@ -502,14 +506,15 @@ __device__ __forceinline__ void first_step(const MgLevel<T> &L, N n, T b0, T b1,
 // Operations: the node's own inputs (load) are requested before the stencil,
 // then op(n, y, inputs, partial sums).
 
-// One Chebyshev step.
-template <typename T>
+// One Chebyshev step.  KEEP: a step of this smoothing follows, and the direction
+// is read from and left in d; otherwise it is read from where x_out goes.
+template <typename T, bool KEEP>
 struct OpSmooth {
   MgLevel<T> L;
-  V3<T> b, xin, xout;
+  V3<T> b, xin, xout, d;
   T c1, c2;
-  int from;
-  struct Pre { T b[3], D[6], p[3], x[3]; };
+  int dir;
+  struct Pre { T b[3], D[6], d[3], x[3]; };
   __device__ Pre load(int64_t n) const {
     Pre q;
     dinv_load<T>(L, n, q.D);
@@ -517,7 +522,7 @@ struct OpSmooth {
     for (int c = 0; c < 3; ++c) {
       q.b[c] = b.c[c][n];
       q.x[c] = xin.c[c][n];
-      q.p[c] = from == kFromOut ? xout.c[c][n] : T(0);
+      q.d[c] = dir == kDirKept ? (KEEP ? d : xout).c[c][n] : dir == kDirX ? q.x[c] : T(0);
     }
     return q;
   }
@@ -527,7 +532,9 @@ struct OpSmooth {
     dinv_apply<T>(q.D, r, z);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      xout.c[c][n] = q.x[c] + (c2 * z[c] + c1 * (q.x[c] - q.p[c]));
+      const T dn = c2 * z[c] + c1 * q.d[c];
+      if (KEEP) d.c[c][n] = dn;
+      xout.c[c][n] = q.x[c] + dn;
     }
   }
 };
@@ -685,7 +692,7 @@ __global__ __launch_bounds__(576) void mg_stencil_rows_kernel(MgLevel<T> L, V3<T
 
 // b_C = P^T r_F (one thread per coarse node).  With smooth != 0 the coarse
 // level's first Chebyshev step (x = 0, so pointwise) follows at once:
-// d_C = x_C = c2 Dinv_C b_C.
+// x_C = c2 Dinv_C b_C.
 // Three waves per 64 coarse nodes, one per fine plane around them: the plane's
 // nine nodes are one round trip to memory (positions are computed, not read
 // from the axis tables first), and the planes are added in a fixed order from
@@ -886,37 +893,44 @@ __global__ __launch_bounds__(kDenseRows * kDenseParts) void mg_dense_kernel(cons
 
 // ---- level 0 on the cell-based HEX8 apply -----------------------------------------
 
-// Chebyshev step on level 0 (x_in = the applied vector).
-template <typename T>
+// Chebyshev step on level 0 (x_in = the applied vector); KEEP as in OpSmooth.
+template <typename T, bool KEEP>
 struct EpiSmooth0 {
   MgLevel<T> L;
-  V3<T> b, xout;
+  V3<T> b, xout, d;
   T c1, c2;
-  int from;
-  struct Pre { T b[3], D[6], p[3]; };
+  int dir;
+  struct Pre { T b[3], D[6], d[3]; };
   __device__ Pre load(NodeAt n) const {
     Pre q;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       q.b[c] = ld(b.c[c], n);
-      q.p[c] = T(0);
+      q.d[c] = T(0);
     }
     dinv_load<T>(L, n, q.D);
-    if (from == kFromOut) {
+    if (dir == kDirKept) {
       n.off = fresh(n.off);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) q.p[c] = ld(xout.c[c], n);
+      for (int c = 0; c < 3; ++c) q.d[c] = ld((KEEP ? d : xout).c[c], n);
     }
     return q;
   }
-  __device__ void operator()(NodeAt n, const T y[3], const T xc[3], const Pre &q, double *) const {
+  __device__ void step(NodeAt n, const T y[3], const T xc[3], const Pre &q, T xo[3]) const {
     const T r[3] = {q.b[0] - y[0], q.b[1] - y[1], q.b[2] - y[2]};
     T z[3];
     dinv_apply<T>(q.D, r, z);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      st(xout.c[c], n, xc[c] + (c2 * z[c] + c1 * (xc[c] - q.p[c])));
+      const T dn = c2 * z[c] + c1 * (dir == kDirX ? xc[c] : q.d[c]);
+      if (KEEP) st(d.c[c], n, dn);
+      xo[c] = xc[c] + dn;
+      st(xout.c[c], n, xo[c]);
     }
+  }
+  __device__ void operator()(NodeAt n, const T y[3], const T xc[3], const Pre &q, double *) const {
+    T xo[3];
+    step(n, y, xc, q, xo);
   }
 };
 
@@ -924,18 +938,13 @@ struct EpiSmooth0 {
 // b = r: also the dot product r . z of the result z = x_out (per-block sums
 // into the partials), so no separate pass reads r and z again.
 template <typename T>
-struct EpiSmooth0Dot : EpiSmooth0<T> {
-  __device__ void operator()(NodeAt n, const T y[3], const T xc[3], const typename EpiSmooth0<T>::Pre &q,
+struct EpiSmooth0Dot : EpiSmooth0<T, false> {
+  __device__ void operator()(NodeAt n, const T y[3], const T xc[3], const typename EpiSmooth0<T, false>::Pre &q,
                              double *red) const {
-    const T r[3] = {q.b[0] - y[0], q.b[1] - y[1], q.b[2] - y[2]};
-    T z[3];
-    dinv_apply<T>(q.D, r, z);
+    T xo[3];
+    this->step(n, y, xc, q, xo);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const T xo = xc[c] + (this->c2 * z[c] + this->c1 * (xc[c] - q.p[c]));
-      st(this->xout.c[c], n, xo);
-      red[0] += double(q.b[c]) * double(xo);
-    }
+    for (int c = 0; c < 3; ++c) red[0] += double(q.b[c]) * double(xo[c]);
   }
 };
 
@@ -1130,15 +1139,19 @@ inline int64_t stencil_blocks(const MgLevel<T> &L) {
   return L.n <= kRowsMax ? (L.n + 63) / 64 : lblocks(L);
 }
 
+// Smoothing step `step` on level l from xin to xout; keep: the direction goes to d.
 template <typename T>
-hipError_t smooth(const MgDev<T> &G, int l, V3<T> b, V3<T> xin, V3<T> xout, int step, int from,
-                  const DevScalars *sc, hipStream_t s, double *dot_partials = nullptr) {
+hipError_t smooth(const MgDev<T> &G, int l, V3<T> b, V3<T> xin, V3<T> xout, V3<T> d, int step, int dir, bool keep,
+                  const DevScalars *sc, hipStream_t s, double *dot_partials) {
   const MgLevel<T> &L = G.L[l];
   const T c1 = T(L.c1[step]), c2 = T(L.c2[step]);
   if (l == 0 && dot_partials)
-    return launch_hex8<T, 1>(G.M, xin.c, EpiSmooth0Dot<T>{{L, b, xout, c1, c2, from}}, dot_partials, sc, s);
-  if (l == 0) return launch_hex8<T, 0>(G.M, xin.c, EpiSmooth0<T>{L, b, xout, c1, c2, from}, nullptr, sc, s);
-  return launch_stencil<T, 0>(L, xin, OpSmooth<T>{L, b, xin, xout, c1, c2, from}, nullptr, sc, s);
+    return launch_hex8<T, 1>(G.M, xin.c, EpiSmooth0Dot<T>{{L, b, xout, d, c1, c2, dir}}, dot_partials, sc, s);
+  if (l == 0 && keep)
+    return launch_hex8<T, 0>(G.M, xin.c, EpiSmooth0<T, true>{L, b, xout, d, c1, c2, dir}, nullptr, sc, s);
+  if (l == 0) return launch_hex8<T, 0>(G.M, xin.c, EpiSmooth0<T, false>{L, b, xout, d, c1, c2, dir}, nullptr, sc, s);
+  if (keep) return launch_stencil<T, 0>(L, xin, OpSmooth<T, true>{L, b, xin, xout, d, c1, c2, dir}, nullptr, sc, s);
+  return launch_stencil<T, 0>(L, xin, OpSmooth<T, false>{L, b, xin, xout, d, c1, c2, dir}, nullptr, sc, s);
 }
 
 // Coarse levels get their first smoothing step inside the restriction, and
@@ -1158,11 +1171,16 @@ hipError_t vcycle_level(const MgDev<T> &G, int l, V3<T> b, const DevScalars *sc,
     *out = L.xa;
     return hipGetLastError();
   }
-  V3<T> xc = L.xa, xo = L.xb;
-  for (int k = 1; k < L.deg; ++k) {
-    if ((e = smooth(G, l, b, xc, xo, k, k == 1 ? kFromZero : kFromOut, sc, s)) != hipSuccess) return e;
-    std::swap(xc, xo);
-  }
+  V3<T> xc = L.xa, xo = L.xb, d = L.d;
+  auto step = [&](int k, int dir, double *dp) {
+    const bool keep = k + 1 < L.deg;
+    V3<T> &to = !keep && dir == kDirKept ? d : xo;
+    const hipError_t err = smooth(G, l, b, xc, to, d, k, dir, keep, sc, s, dp);
+    std::swap(xc, to);
+    return err;
+  };
+  for (int k = 1; k < L.deg; ++k)
+    if ((e = step(k, k == 1 ? kDirX : kDirKept, nullptr)) != hipSuccess) return e;
   e = l == 0 ? launch_hex8<T, 0>(G.M, xc.c, EpiResid0<T>{b, xo}, nullptr, sc, s)
              : launch_stencil<T, 0>(L, xc, OpResid<T>{b, xo}, nullptr, sc, s);
   if (e != hipSuccess) return e;
@@ -1176,12 +1194,10 @@ hipError_t vcycle_level(const MgDev<T> &G, int l, V3<T> b, const DevScalars *sc,
   dim3 gp = lgrid(L);
   gp.z = (gp.z + kProlong - 1) / kProlong;
   hipLaunchKernelGGL((mg_prolong_kernel<T>), gp, dim3(BX, BY), 0, s, L, xc, C, xcoarse, sc);
-  for (int k = 0; k < L.deg; ++k) {
-    // with dot_partials (level 0 of a CG step): the last step also forms b . out
-    double *dp = (l == 0 && k + 1 == L.deg) ? dot_partials : nullptr;
-    if ((e = smooth(G, l, b, xc, xo, k, k == 0 ? kFromNone : kFromOut, sc, s, dp)) != hipSuccess) return e;
-    std::swap(xc, xo);
-  }
+  // with dot_partials (level 0 of a CG step): the last step also forms b . out
+  for (int k = 0; k < L.deg; ++k)
+    if ((e = step(k, k == 0 ? kDirNone : kDirKept, l == 0 && k + 1 == L.deg ? dot_partials : nullptr)) != hipSuccess)
+      return e;
   *out = xc;
   return hipGetLastError();
 }

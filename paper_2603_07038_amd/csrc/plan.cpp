@@ -512,6 +512,7 @@ etm_status derive(etm_plan *p, const etm_source *src) {
       take(L.dead, n);
       take(L.xa, 3 * n * tsz);
       take(L.xb, 3 * n * tsz);
+      take(L.d, 3 * n * tsz);
       if (l > 0) take(L.b, 3 * n * tsz);
     }
     const MgHostLevel &C = p->mg.back();
@@ -798,7 +799,7 @@ MgDev<T> mg_dev(const etm_plan *p) {
         for (int c = 0; c < 3; ++c) v.c[c] = p->ptr<T>(r) + c * H.n;
       return v;
     };
-    L.xa = v3(H.xa); L.xb = v3(H.xb); L.b = v3(H.b);
+    L.xa = v3(H.xa); L.xb = v3(H.xb); L.d = v3(H.d); L.b = v3(H.b);
     for (int a = 0; a < 3; ++a) {
       L.ax[a].lo = reinterpret_cast<const int32_t *>(tb + H.tab[a][0]);
       L.ax[a].w = reinterpret_cast<const double *>(tb + H.tab[a][1]);

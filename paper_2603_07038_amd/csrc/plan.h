@@ -42,7 +42,7 @@ using namespace etm;
 struct MgHostLevel {
   int nx = 0, ny = 0, nz = 0;          // cells
   int64_t sy = 0, sz = 0, n = 0;       // node strides, entries per vector component
-  Region A, Dinv, dead, xa, xb, b;  // device regions (A: coarse levels only)
+  Region A, Dinv, dead, xa, xb, d, b;  // device regions (A: coarse levels only)
   size_t tab[3][3] = {};               // offsets in r_mgtab of lo, w, cpos per axis (from level + 1)
   int deg = 2;
   double c1[kMgDeg] = {}, c2[kMgDeg] = {};

@@ -62,3 +62,22 @@ def test_both_stencil_kernels_precondition_alike(nz):
         assert np.linalg.norm(res) <= 2e-10 * np.linalg.norm(f)
     # refinement restarts cost the mixed path a few iterations, no more
     assert its[1] <= its[0] + 16 and max(its) <= 60
+
+
+# smoothing degrees: a step that reads no direction, one that takes x for it, and
+# (from 3 on) ones that read and store it, with the three vectors of a level
+# changing places; both preconditioners are symmetric, so CG gets there
+@pytest.mark.parametrize("precision", [etm.ETM_PREC_FP64, etm.ETM_PREC_MIXED])
+@pytest.mark.parametrize("degree", [(1, 1), (2, 1), (3, 2), (4, 3), (1, 4)])
+def test_every_smoothing_degree_converges(degree, precision):
+    prob = W.random_problem(58, 40, 33, 9, n_steps=4, R=2, n_ports=1, void_top=0, mech_bc=W.MECH_CLAMP_ZMIN)
+    prob.cg_rtol = 1e-10
+    th = np.random.default_rng(3).uniform(0.0, 40.0, (prob.nz + 1, prob.ny + 1, prob.nx + 1))
+    plan, info = _solve(prob, th, precision, mg_coarse_dofs=60, mg_degree=degree)
+    assert info["mg_levels"] >= 3 and info["cg_relres"] <= prob.cg_rtol
+    jac = _solve(prob, th, precision, mech_precond=etm.ETM_PRECOND_JACOBI)[1]
+    assert info["cg_iters"] <= jac["cg_iters"] / 2
+    o = oracle.Oracle(prob)
+    f = o.mech_rhs(th, o.mech_mask())
+    res = f - o.mech_apply(o.mech_mask(), plan.u())
+    assert np.linalg.norm(res) <= 2e-10 * np.linalg.norm(f)
