@@ -295,12 +295,16 @@ void etm_plan_destroy(etm_plan *plan);
  * tune_json (NULL or "{}": defaults) is the autotuner's table of tile shapes
  * per size class, the class being floor(log2(cells)) of a variant:
  *   {"kchunk": {"<class>": planes, ...}, "layout": {"<class>": 1 | 2, ...},
- *    "kchunk_fp64": {"<class>": planes, ...}}
+ *    "kchunk_fp64": {"<class>": planes, ...}, "limit_kchunk": {"<class>": planes, ...}}
  * kchunk (1..128) is the z-chunk of the mixed-precision march tiles and
  * kchunk_fp64 that of the FP64 tiles; layout (mixed precision only) makes
  * the waves take runs of 62 nodes over the plane numbered x fastest (1) or
  * rows of tiles of 64 x 4 nodes staged in LDS (2).  A class without an entry
- * takes the chunk and layout the library picks from the variant.  Entries
+ * takes the chunk and layout the library picks from the variant.
+ * limit_kchunk (mixed precision) is read by etm_batch_advance_noalloc alone:
+ * a variant of the class counts against its limit as runs of that z-chunk,
+ * whatever it is launched as, so that a table timed again does not change
+ * what the call accepts; a class without an entry counts as launched.  Entries
  * out of range and malformed text are ignored; no choice changes results.
  * The string is read at creation and not kept. */
 etm_status etm_batch_create(int32_t max_slots, const char *tune_json, etm_batch **out);
@@ -318,8 +322,10 @@ etm_status etm_batch_advance(etm_batch *batch, int64_t n_em_steps, void *hip_str
  * hipMalloc / hipFree / graph instantiation; the batch and its plans must
  * already exist and be bound.
  * Limits (ETM_E_INVAL beyond them, nothing enqueued): at most 64 attached
- * variants; at most 259,344 march tiles over all variants (counted as 62 x 4
- * nodes by one z-chunk in mixed precision, 64 x 4 in FP64); attached plans
+ * variants; at most 259,344 march tiles over all variants (counted as runs of
+ * 248 nodes of a plane by one z-chunk in mixed precision, as 62 x 4 nodes for
+ * rows of 1024 nodes and more and for layout 2 without a limit_kchunk, and as
+ * 64 x 4 nodes in FP64); attached plans
  * must not schedule mechanical solves (mech_every_thermal = 0); every plan's
  * workspace must be on the device that was current at etm_batch_create.
  * The array is shared by every call on one GPU and keeps the last call's

@@ -16,7 +16,8 @@
 // its work layout (runs over the x-fastest plane or tiles) -- comes
 // from a tuning table keyed by the variant's size class
 // ("{\"kchunk\": {\"<log2 cells>\": k, ...}, \"layout\": {\"<log2 cells>\": 1 or 2},
-// \"kchunk_fp64\": {...}}"; "kchunk" serves mixed precision),
+// \"kchunk_fp64\": {...}, \"limit_kchunk\": {...}}"; "kchunk" serves mixed precision,
+// "limit_kchunk" the limit of the allocation-free advance),
 // written by the package's autotuner; without an entry the automatic choice
 // is used.
 //
@@ -50,6 +51,7 @@ struct etm_batch {
   std::map<int, int> kchunk_by_class;       // mixed precision
   std::map<int, int> kchunk_fp64_by_class;  // FP64
   std::map<int, int> layout_by_class;
+  std::map<int, int> limit_kchunk_by_class;  // mixed precision, see limit_kchunk()
   // device
   BatchVar *d_vars = nullptr;
   int4 *d_items = nullptr;
@@ -126,6 +128,14 @@ void order_variants(etm_batch *b) {
     auto it = km.find(size_class(p));
     p->kchunk = it != km.end() ? it->second : em_kchunk(p->dev_grid(), b->precision, false);
   }
+}
+
+// The z-chunk at which the allocation-free advance counts a variant's runs
+// against its limit, or 0: counted as it is launched.
+int limit_kchunk(const etm_batch *b, const etm_plan *p) {
+  if (b->precision != ETM_PREC_MIXED) return 0;
+  auto it = b->limit_kchunk_by_class.find(size_class(p));
+  return it != b->limit_kchunk_by_class.end() ? it->second : 0;
 }
 
 // New work list after attach / detach.  Kernels and graph launches of the
@@ -379,6 +389,7 @@ etm_status etm_batch_create(int32_t max_slots, const char *tune_json, etm_batch 
   b->old_cur.assign(max_slots, 0);
   parse_tune(tune_json, "\"kchunk\"", 1, 128, b->kchunk_by_class);
   parse_tune(tune_json, "\"kchunk_fp64\"", 1, 128, b->kchunk_fp64_by_class);
+  parse_tune(tune_json, "\"limit_kchunk\"", 1, 128, b->limit_kchunk_by_class);
   parse_tune(tune_json, "\"layout\"", kLayoutRuns, kLayoutTiles, b->layout_by_class);
   hipError_t e = hipGetDevice(&b->device);
   if (e == hipSuccess) e = hipMalloc((void **)&b->d_vars, sizeof(BatchVar) * max_slots);
@@ -452,29 +463,58 @@ etm_status etm_batch_advance_noalloc(etm_batch *b, int64_t n, void *stream) {
     return fail(ETM_E_INVAL, "no-alloc advance: " + std::to_string(n_att) + " attached variants, at most " +
                                  std::to_string(kScratchSlots));
   if (n_att == 0 || n == 0) return ETM_OK;
-  // the work list of the current set (the graph path's list is left as it is)
+  // the work list of the current set (the graph path's list is left as it is).
+  // What the limit accepts must not change when the tuning table is timed again,
+  // so a variant with a limit_kchunk is counted in runs of that chunk; where the
+  // table's own choice then needs more room than there is, such variants are
+  // launched as they are counted (every choice gives the same results).
   order_variants(b);
   ItemTable T;
   std::memset(&T, 0, sizeof(T));
   T.n_var = int(b->order.size());
-  int64_t total = 0, counted = 0;
-  for (int v = 0; v < T.n_var; ++v) {
-    etm_plan *p = b->slots[b->order[v]];
+  int64_t counted = 0;
+  for (int slot : b->order) {
+    etm_plan *p = b->slots[slot];
     hipPointerAttribute_t attr;
     HIP_TRY(hipPointerGetAttributes(&attr, p->ws));
     if (attr.device != b->device)
       return fail(ETM_E_INVAL, "no-alloc advance: a plan's workspace is not on the batch's device");
-    int ntx, nty, nkc;
-    em_tiles(p->dev_grid(), b->precision, p->kchunk, &ntx, &nty, &nkc);
-    T.prefix[v] = int(total);
-    T.ntx[v] = ntx;
-    T.nty[v] = nty;
-    total += int64_t(ntx) * nty * nkc;
-    counted += em_list_tiles(p->dev_grid(), b->precision, p->kchunk);
+    DevGrid g = p->dev_grid();
+    const int lim = limit_kchunk(b, p);
+    if (lim) g.layout = kLayoutRuns;
+    counted += em_list_tiles(g, b->precision, lim ? lim : p->kchunk);
     if (counted > kScratchMaxItems)
       return fail(ETM_E_INVAL, "no-alloc advance: the work list exceeds " + std::to_string(kScratchMaxItems) +
                                    " tiles (" + std::to_string(kScratchBytes) + " bytes of scratch)");
   }
+  int64_t total = 0;
+  auto lay_out = [&] {
+    total = 0;
+    for (int v = 0; v < T.n_var; ++v) {
+      etm_plan *p = b->slots[b->order[v]];
+      int ntx, nty, nkc;
+      em_tiles(p->dev_grid(), b->precision, p->kchunk, &ntx, &nty, &nkc);
+      T.prefix[v] = int(std::min<int64_t>(total, INT32_MAX));
+      T.ntx[v] = ntx;
+      T.nty[v] = nty;
+      total += int64_t(ntx) * nty * nkc;
+    }
+  };
+  lay_out();
+  const bool as_counted = total > 2 * kScratchMaxItems;
+  if (as_counted) {
+    for (int slot : b->order)
+      if (const int lim = limit_kchunk(b, b->slots[slot])) {
+        b->slots[slot]->layout = kLayoutRuns;
+        b->slots[slot]->kchunk = lim;
+      }
+    lay_out();
+  }
+  // the shapes of the graph path's list again, whatever this call returns
+  struct Restore {
+    etm_batch *b;
+    ~Restore() { if (b) order_variants(b); }
+  } restore{as_counted ? b : nullptr};
   T.prefix[T.n_var] = int(total);
   char *base = nullptr;
   etm_status s = scratch_on(b->device, &base);

@@ -18,7 +18,9 @@ EM steps.  The choice per class (see ``pick``) is written as
 "timings_us": {...}, "timings_fp64_us": {...}}`` (a run updates its own
 precision's entries), the table ``Batch`` reads (``tune_gfx950.json`` next to
 this file by default).  Every layout and chunk gives bitwise the same
-results, so the table changes speed only.
+results, so the table changes speed only: ``"limit_kchunk"``, by which the
+allocation-free advance counts a variant's tiles against its limit, is kept
+as it is, so that no picks change what that call accepts.
 
 An FP64 run records its timings but writes its picks (``"kchunk_fp64"``)
 only with ``--fp64-map``: on gfx950 the FP64 chunks are within 1 % of each

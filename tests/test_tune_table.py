@@ -66,3 +66,17 @@ def test_shipped_table_is_well_formed():
         best = min(row.values())
         key = f"{'runs' if lay == 1 else 'rows'}/{kc}"
         assert row[key] <= (1.0 + tune.TIE) * best + 1e-9, (c, key)
+
+
+def test_limit_chunks_outlive_a_new_tuning(tmp_path, monkeypatch):
+    with open(tune.DEFAULT_TABLE) as f:
+        shipped = json.load(f)
+    # what the allocation-free advance counts with, from the first table on
+    assert shipped["limit_kchunk"] == {"15": 2, "16": 4, "17": 6, "18": 12, "19": 12, "20": 6, "21": 4, "22": 6,
+                                       "23": 6, "24": 6}
+    monkeypatch.setattr(tune, "time_class", _fake_time_class)
+    out = tmp_path / "t.json"
+    out.write_text(json.dumps(shipped))
+    tune.main(["--out", str(out), "--classes", "15-24", "--precision", "mixed"])
+    t = json.loads(out.read_text())
+    assert t["kchunk"] != shipped["kchunk"] and t["limit_kchunk"] == shipped["limit_kchunk"]

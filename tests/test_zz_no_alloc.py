@@ -88,3 +88,38 @@ def test_noalloc_rejects_beyond_its_limits():
         b.advance_noalloc(4)
     assert ei.value.status == etm.ETM_E_INVAL and "mech_every_thermal" in str(ei.value)
     assert pl.sync()["step"] == 0
+
+
+def test_noalloc_accepts_what_the_limit_counts_with_the_default_table():
+    """Columns of 8 x 8 nodes and 20,901 planes: 38 of them count 66,196 runs
+    of 12 planes; as the tiles of 6 planes that the default table launches
+    (264,784 of them) they would not be accepted.  The list of another batch,
+    with a chunk of 1 plane, has no room and is launched as it is counted."""
+    p = W.random_problem(77, 7, 7, 20900, n_steps=4, R=2, n_ports=2, amp=3e10, em_bc=(0,) * 6)
+    dt = etm.cfl_dt(p)
+    J = p.sample_J_half(dt, 4)
+
+    def plan():
+        return etm.Plan(p, J, dt=dt, precision=etm.ETM_PREC_MIXED, n_steps=4, history=False)
+
+    def state(pl):
+        return [pl.read(f) for f in FIELDS]
+
+    ref = plan()
+    ref.advance(4)
+    ref.sync()
+    want = state(ref)
+    plans = [plan() for _ in range(38)]
+    for table, calls in ((None, (2,)), ('{"kchunk": {"19": 1}, "layout": {"19": 2}, "limit_kchunk": {"19": 12}}', (1, 1))):
+        b = etm.Batch(38, table)
+        for pl in plans:
+            b.attach(pl)
+        for n in calls:
+            b.advance_noalloc(n)
+        for slot in range(38):
+            b.detach(slot)
+        del b
+    for pl in (plans[0], plans[-1]):
+        assert pl.sync()["step"] == 4
+        for a, w in zip(state(pl), want):
+            np.testing.assert_array_equal(a, w)
