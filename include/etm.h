@@ -302,9 +302,9 @@ void etm_plan_destroy(etm_plan *plan);
  * rows of tiles of 64 x 4 nodes staged in LDS (2).  A class without an entry
  * takes the chunk and layout the library picks from the variant.
  * limit_kchunk (mixed precision) is read by etm_batch_advance_noalloc alone:
- * a variant of the class counts against its limit as runs of that z-chunk,
- * whatever it is launched as, so that a table timed again does not change
- * what the call accepts; a class without an entry counts as launched.  Entries
+ * a variant of the class may also count against its limit as runs of that
+ * z-chunk, whatever it is launched as, so that a table timed again still
+ * accepts what the one before did.  Entries
  * out of range and malformed text are ignored; no choice changes results.
  * The string is read at creation and not kept. */
 etm_status etm_batch_create(int32_t max_slots, const char *tune_json, etm_batch **out);
@@ -324,8 +324,9 @@ etm_status etm_batch_advance(etm_batch *batch, int64_t n_em_steps, void *hip_str
  * Limits (ETM_E_INVAL beyond them, nothing enqueued): at most 64 attached
  * variants; at most 259,344 march tiles over all variants (counted as runs of
  * 248 nodes of a plane by one z-chunk in mixed precision, as 62 x 4 nodes for
- * rows of 1024 nodes and more and for layout 2 without a limit_kchunk, and as
- * 64 x 4 nodes in FP64); attached plans
+ * rows of 1024 nodes and more and for layout 2, and as 64 x 4 nodes in FP64;
+ * or, if that total is smaller, with every variant of a class that has a
+ * limit_kchunk counted as runs of that chunk); attached plans
  * must not schedule mechanical solves (mech_every_thermal = 0); every plan's
  * workspace must be on the device that was current at etm_batch_create.
  * The array is shared by every call on one GPU and keeps the last call's

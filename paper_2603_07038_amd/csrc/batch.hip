@@ -464,15 +464,16 @@ etm_status etm_batch_advance_noalloc(etm_batch *b, int64_t n, void *stream) {
                                  std::to_string(kScratchSlots));
   if (n_att == 0 || n == 0) return ETM_OK;
   // the work list of the current set (the graph path's list is left as it is).
-  // What the limit accepts must not change when the tuning table is timed again,
-  // so a variant with a limit_kchunk is counted in runs of that chunk; where the
+  // What the limit accepts must not shrink when the tuning table is timed again,
+  // so the tiles are counted as they are launched and, for variants with a
+  // limit_kchunk, in runs of that chunk, and the smaller total counts; where the
   // table's own choice then needs more room than there is, such variants are
-  // launched as they are counted (every choice gives the same results).
+  // launched as those runs (every choice gives the same results).
   order_variants(b);
   ItemTable T;
   std::memset(&T, 0, sizeof(T));
   T.n_var = int(b->order.size());
-  int64_t counted = 0;
+  int64_t launched = 0, counted = 0;
   for (int slot : b->order) {
     etm_plan *p = b->slots[slot];
     hipPointerAttribute_t attr;
@@ -480,10 +481,12 @@ etm_status etm_batch_advance_noalloc(etm_batch *b, int64_t n, void *stream) {
     if (attr.device != b->device)
       return fail(ETM_E_INVAL, "no-alloc advance: a plan's workspace is not on the batch's device");
     DevGrid g = p->dev_grid();
+    const int64_t tiles = em_list_tiles(g, b->precision, p->kchunk);
     const int lim = limit_kchunk(b, p);
     if (lim) g.layout = kLayoutRuns;
-    counted += em_list_tiles(g, b->precision, lim ? lim : p->kchunk);
-    if (counted > kScratchMaxItems)
+    launched += tiles;
+    counted += lim ? em_list_tiles(g, b->precision, lim) : tiles;
+    if (std::min(launched, counted) > kScratchMaxItems)
       return fail(ETM_E_INVAL, "no-alloc advance: the work list exceeds " + std::to_string(kScratchMaxItems) +
                                    " tiles (" + std::to_string(kScratchBytes) + " bytes of scratch)");
   }

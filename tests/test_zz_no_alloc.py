@@ -94,7 +94,8 @@ def test_noalloc_accepts_what_the_limit_counts_with_the_default_table():
     """Columns of 8 x 8 nodes and 20,901 planes: 38 of them count 66,196 runs
     of 12 planes; as the tiles of 6 planes that the default table launches
     (264,784 of them) they would not be accepted.  The list of another batch,
-    with a chunk of 1 plane, has no room and is launched as it is counted."""
+    with a chunk of 1 plane, has no room and is launched as it is counted.  A
+    table whose launch is the smaller count is accepted by that."""
     p = W.random_problem(77, 7, 7, 20900, n_steps=4, R=2, n_ports=2, amp=3e10, em_bc=(0,) * 6)
     dt = etm.cfl_dt(p)
     J = p.sample_J_half(dt, 4)
@@ -110,7 +111,8 @@ def test_noalloc_accepts_what_the_limit_counts_with_the_default_table():
     ref.sync()
     want = state(ref)
     plans = [plan() for _ in range(38)]
-    for table, calls in ((None, (2,)), ('{"kchunk": {"19": 1}, "layout": {"19": 2}, "limit_kchunk": {"19": 12}}', (1, 1))):
+    for table, calls in ((None, (2,)), ('{"kchunk": {"19": 1}, "layout": {"19": 2}, "limit_kchunk": {"19": 12}}', (1,)),
+                         ('{"kchunk": {"19": 8}, "layout": {"19": 1}, "limit_kchunk": {"19": 1}}', (1,))):
         b = etm.Batch(38, table)
         for pl in plans:
             b.attach(pl)
@@ -119,6 +121,12 @@ def test_noalloc_accepts_what_the_limit_counts_with_the_default_table():
         for slot in range(38):
             b.detach(slot)
         del b
+    b = etm.Batch(38, '{"kchunk": {"19": 1}, "layout": {"19": 2}, "limit_kchunk": {"19": 1}}')
+    for pl in plans:
+        b.attach(pl)
+    with pytest.raises(etm.EtmError) as ei:  # too many either way
+        b.advance_noalloc(1)
+    assert ei.value.status == etm.ETM_E_INVAL and "exceeds" in str(ei.value)
     for pl in (plans[0], plans[-1]):
         assert pl.sync()["step"] == 4
         for a, w in zip(state(pl), want):
