@@ -295,12 +295,15 @@ void etm_plan_destroy(etm_plan *plan);
  * tune_json (NULL or "{}": defaults) is the autotuner's table of tile shapes
  * per size class, the class being floor(log2(cells)) of a variant:
  *   {"kchunk": {"<class>": planes, ...}, "layout": {"<class>": 1 | 2, ...},
- *    "kchunk_fp64": {"<class>": planes, ...}, "limit_kchunk": {"<class>": planes, ...}}
+ *    "kchunk_fp64": {"<class>": planes, ...}, "limit_kchunk": {"<class>": planes, ...},
+ *    "min_nodes": nodes}
  * kchunk (1..128) is the z-chunk of the mixed-precision march tiles and
  * kchunk_fp64 that of the FP64 tiles; layout (mixed precision only) makes
  * the waves take runs of 62 nodes over the plane numbered x fastest (1) or
  * rows of tiles of 64 x 4 nodes staged in LDS (2).  A class without an entry
- * takes the chunk and layout the library picks from the variant.
+ * takes the chunk and layout the library picks from the variant, and so does
+ * every mixed-precision variant while the attached plans have fewer than
+ * min_nodes nodes in all (rows padded to 16; 0 without the entry).
  * limit_kchunk (mixed precision) is read by etm_batch_advance_noalloc alone:
  * a variant of the class may also count against its limit as runs of that
  * z-chunk, whatever it is launched as, so that a table timed again still

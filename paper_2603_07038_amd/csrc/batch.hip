@@ -18,8 +18,8 @@
 // ("{\"kchunk\": {\"<log2 cells>\": k, ...}, \"layout\": {\"<log2 cells>\": 1 or 2},
 // \"kchunk_fp64\": {...}, \"limit_kchunk\": {...}}"; "kchunk" serves mixed precision,
 // "limit_kchunk" the limit of the allocation-free advance),
-// written by the package's autotuner; without an entry the automatic choice
-// is used.
+// written by the package's autotuner; without an entry, and in batches of fewer
+// nodes than the table's "min_nodes", the automatic choice is used.
 //
 // etm_batch_advance_noalloc runs the same steps with the same kernels but
 // allocates nothing: the descriptors and the work list live
@@ -52,6 +52,7 @@ struct etm_batch {
   std::map<int, int> kchunk_fp64_by_class;  // FP64
   std::map<int, int> layout_by_class;
   std::map<int, int> limit_kchunk_by_class;  // mixed precision, see limit_kchunk()
+  int min_nodes = 0;  // mixed precision: the table holds for batches of at least that many nodes
   // device
   BatchVar *d_vars = nullptr;
   int4 *d_items = nullptr;
@@ -108,6 +109,18 @@ void parse_tune(const char *json, const char *name, int lo, int hi, std::map<int
   }
 }
 
+// One integer of the tuning table, {"name": value}; 0 without it.
+int parse_tune_value(const char *json, const char *name) {
+  if (!json) return 0;
+  const std::string s(json);
+  size_t p = s.find(name);
+  if (p == std::string::npos) return 0;
+  p = s.find_first_not_of(" \t\r\n", p + std::strlen(name));
+  if (p == std::string::npos || s[p] != ':') return 0;
+  const long long v = std::atoll(s.c_str() + p + 1);
+  return int(std::max(0ll, std::min<long long>(v, INT32_MAX)));
+}
+
 int size_class(const etm_plan *p) {
   const double cells = double(p->nx) * p->ny * p->nz;
   return int(std::floor(std::log2(std::max(cells, 1.0))));
@@ -115,18 +128,28 @@ int size_class(const etm_plan *p) {
 
 // Compact list of the attached slots (b->order keeps its capacity of
 // max_slots from creation, so this allocates nothing) and each variant's
-// z-chunk from the tuning table.
+// layout and z-chunk: from the tuning table, whose classes are timed in batches
+// that stream from HBM, if the batch has that many nodes; otherwise the
+// library's own choice (runs, and chunks short enough to fill the GPU).  us per
+// mixed step, table | own choice, for 1, 2 and 4 variants of
+//   40x40x33    23.4 | 13.6  23.1 | 14.1   22.9 | 14.4
+//   180x170x45  44.4 | 30.1  64.5 | 61.2   120 | 140 (5.7 M nodes)
+// and twelve uneven ones 186 | 200.
 void order_variants(etm_batch *b) {
   b->order.clear();
   for (int s = 0; s < b->max_slots; ++s)
     if (b->slots[s]) b->order.push_back(s);
+  const bool mixed = b->precision == ETM_PREC_MIXED;
+  int64_t nodes = 0;
+  for (int slot : b->order) nodes += b->slots[slot]->ntot;
+  const bool table = !mixed || nodes >= b->min_nodes;
+  const std::map<int, int> &km = mixed ? b->kchunk_by_class : b->kchunk_fp64_by_class;
   for (int slot : b->order) {
     etm_plan *p = b->slots[slot];
     auto lt = b->layout_by_class.find(size_class(p));
-    p->layout = lt != b->layout_by_class.end() ? lt->second : kLayoutAuto;
-    const std::map<int, int> &km = b->precision == ETM_PREC_FP64 ? b->kchunk_fp64_by_class : b->kchunk_by_class;
+    p->layout = table && lt != b->layout_by_class.end() ? lt->second : kLayoutAuto;
     auto it = km.find(size_class(p));
-    p->kchunk = it != km.end() ? it->second : em_kchunk(p->dev_grid(), b->precision, false);
+    p->kchunk = table && it != km.end() ? it->second : em_kchunk(p->dev_grid(), b->precision, false);
   }
 }
 
@@ -390,6 +413,7 @@ etm_status etm_batch_create(int32_t max_slots, const char *tune_json, etm_batch 
   parse_tune(tune_json, "\"kchunk\"", 1, 128, b->kchunk_by_class);
   parse_tune(tune_json, "\"kchunk_fp64\"", 1, 128, b->kchunk_fp64_by_class);
   parse_tune(tune_json, "\"limit_kchunk\"", 1, 128, b->limit_kchunk_by_class);
+  b->min_nodes = parse_tune_value(tune_json, "\"min_nodes\"");
   parse_tune(tune_json, "\"layout\"", kLayoutRuns, kLayoutTiles, b->layout_by_class);
   hipError_t e = hipGetDevice(&b->device);
   if (e == hipSuccess) e = hipMalloc((void **)&b->d_vars, sizeof(BatchVar) * max_slots);

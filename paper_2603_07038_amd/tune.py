@@ -15,12 +15,16 @@ package variant of that size is replicated until the batch holds at least
 16 M cells, and every candidate (layout, chunk) is timed over graph-replayed
 EM steps.  The choice per class (see ``pick``) is written as
 ``{"kchunk": {"<class>": k, ...}, "layout": {"<class>": 1 or 2, ...},
-"timings_us": {...}, "timings_fp64_us": {...}}`` (a run updates its own
+"min_nodes": n, "timings_us": {...}, "timings_fp64_us": {...}}`` (a run updates its own
 precision's entries), the table ``Batch`` reads (``tune_gfx950.json`` next to
 this file by default).  Every layout and chunk gives bitwise the same
 results, so the table changes speed only: ``"limit_kchunk"``, by which the
 allocation-free advance counts a variant's tiles against its limit, is kept
-as it is, so that no picks change what that call accepts.
+as it is, so that no picks change what that call accepts.  The mixed picks
+hold for batches that stream from HBM, as the timed ones do; in batches of
+fewer than ``min_nodes`` nodes the library's own choice is faster (one
+40x40x33 variant 13.6 us per step against 23.4, one 180x170x45 30.1 against
+44.4).  In the timings' keys "runs" is layout 1 and "rows" layout 2.
 
 An FP64 run records its timings but writes its picks (``"kchunk_fp64"``)
 only with ``--fp64-map``: on gfx950 the FP64 chunks are within 1 % of each
@@ -40,6 +44,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_TABLE = os.path.join(HERE, "tune_gfx950.json")
 CANDIDATES = (2, 4, 6, 8, 12, 16, 24, 32)
+MIN_NODES = (1 << 28) // 85 + 1  # a mixed step's 85 bytes per node no longer fit the 256 MB last-level cache
 LAYOUTS = (1, 2)  # mixed precision: runs over the x-fastest plane, tiles
 
 
@@ -137,6 +142,7 @@ def main(argv=None):
     if a.precision == "mixed":
         table["kchunk"] = kmap
         table["layout"] = lmap
+        table["min_nodes"] = MIN_NODES
     elif a.fp64_map:
         table["kchunk_fp64"] = kmap
     table["timings" + sfx + "_us"] = tmap

@@ -84,3 +84,37 @@ def test_batch_detach_and_continue_solo():
     plans[1].advance(25)   # continue solo
     for a, r in zip(_state(plans[1]), _state(ref)):
         np.testing.assert_array_equal(a, r)
+
+
+def test_table_from_a_batch_size_on_keeps_results():
+    """The table's tiles and chunks hold while the batch has min_nodes nodes:
+    three variants have them, two do not, three have them again."""
+    probs = _variants(5)[1:4]
+    nodes = [(-(-(p.nx + 1) // 16) * 16) * (p.ny + 1) * (p.nz + 1) for p in probs]
+    classes = sorted({_size_class(p) for p in probs})
+    table = json.dumps({"kchunk": {str(c): 3 for c in classes}, "layout": {str(c): 2 for c in classes},
+                        "min_nodes": sum(nodes)})
+    dts = [etm.cfl_dt(p) for p in probs]
+    Js = [p.sample_J_half(dt, 60) for p, dt in zip(probs, dts)]
+
+    def mk(q):
+        return etm.Plan(probs[q], Js[q], dt=dts[q], precision=etm.ETM_PREC_MIXED, n_steps=60, history=False)
+
+    solo = [mk(q) for q in range(3)]
+    for pl in solo:
+        pl.advance(30)
+    plans = [mk(q) for q in range(3)]
+    b = etm.Batch(4, table)
+    slots = [b.attach(pl) for pl in plans]
+    b.advance(8)
+    b.detach(slots[2])
+    b.advance(5)
+    b.advance_noalloc(4)
+    plans[2].advance(9)
+    b.attach(plans[2])
+    b.advance_noalloc(6)
+    b.advance(7)
+    for pl, ref in zip(plans, solo):
+        assert pl.sync()["step"] == 30
+        for x, y in zip(_state(pl), _state(ref)):
+            np.testing.assert_array_equal(x, y)

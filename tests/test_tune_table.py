@@ -80,3 +80,14 @@ def test_limit_chunks_outlive_a_new_tuning(tmp_path, monkeypatch):
     tune.main(["--out", str(out), "--classes", "15-24", "--precision", "mixed"])
     t = json.loads(out.read_text())
     assert t["kchunk"] != shipped["kchunk"] and t["limit_kchunk"] == shipped["limit_kchunk"]
+
+
+def test_table_holds_for_batches_that_stream(tmp_path, monkeypatch):
+    # the march's own rule: 85 bytes per node and step against 256 MB
+    with open(tune.DEFAULT_TABLE) as f:
+        t = json.load(f)
+    assert (t["min_nodes"] - 1) * 85 <= 1 << 28 < t["min_nodes"] * 85
+    monkeypatch.setattr(tune, "time_class", _fake_time_class)
+    out = tmp_path / "t.json"
+    tune.main(["--out", str(out), "--classes", "15-15", "--precision", "mixed"])
+    assert json.loads(out.read_text())["min_nodes"] == t["min_nodes"]
