@@ -237,8 +237,13 @@ etm_status stage_vars(etm_batch *b, hipStream_t st, const BatchDev &D) {
 
 etm_status enqueue_steps(etm_batch *b, int len, hipStream_t st, const BatchDev &D) {
   int64_t nodes = 0;
-  for (int slot : b->order) nodes += b->slots[slot]->ntot;
-  for (int q = 0; q < len; ++q) HIP_TRY(launch_em_batched(D.vars, D.items, D.n_items, q, b->precision, nodes, st));
+  bool flat = false;
+  for (int slot : b->order) {
+    nodes += b->slots[slot]->ntot;
+    flat |= b->precision == ETM_PREC_FP64 && em_tile_is_flat(b->slots[slot]->dev_grid());
+  }
+  for (int q = 0; q < len; ++q)
+    HIP_TRY(launch_em_batched(D.vars, D.items, D.n_items, q, b->precision, nodes, flat, st));
   return ETM_OK;
 }
 

@@ -15,8 +15,8 @@
 // coefficients are always formed in FP64 and rounded once.
 //
 // March kernels.  A block owns a column of nodes and marches up a chunk of z
-// planes (FP64: 32 x 8 nodes staged in LDS with a one-node halo; mixed: 64 x 4
-// of them, or barrier-free waves of 62 nodes each).  A node updates the x-,
+// planes (FP64: 32 x 8 or 64 x 4 nodes staged in LDS with a one-node halo; mixed:
+// 64 x 4 of them, or barrier-free waves of 62 nodes each).  A node updates the x-,
 // y- and z-edges that start at it.  The Joule source is gathered one step late: the
 // node sums sigma e^2 L A over its six incident edges of the *input* field
 // e^n, which the stencil already holds, so no edge update is recomputed.
@@ -33,8 +33,8 @@ namespace etm {
 namespace {
 
 constexpr int BX = 64, BY = 4;             // threads per block (x, y)
-constexpr int TX = 32, TY = 8;             // nodes of a march tile (x, y), one per thread
-constexpr int TXH = TX + 2, TYH = TY + 2;  // staged tile with halo
+// nodes of an FP64 march tile (x, y), one per thread: see em_flat
+constexpr int kTileX = 32, kTileY = 8, kFlatX = 64, kFlatY = 4;
 
 // ---- field accessors: value of component c at node offset (di, dj, dk) --
 template <typename T>
@@ -339,11 +339,11 @@ __device__ __forceinline__ double rcp64(double x) {
 }
 
 // LDS of one FP64 block: four e planes (k - 1, k, k + 1 and the one being
-// staged) of the 32 x 8 node column with a one-node halo, and the dual-width
+// staged) of the TX x TY node column with a one-node halo, and the dual-width
 // shares of its columns and rows.  Four blocks fit on a CU.
-template <typename T>
+template <typename T, int TX, int TY>
 struct MarchSmem {
-  T e[4][3][TYH][TXH];
+  T e[4][3][TY + 2][TX + 2];
   double ax[2][TX], ay[2][TY];
 };
 
@@ -427,7 +427,7 @@ __device__ __forceinline__ void st_plane(T *base, int64_t o, uint32_t n, uint32_
 }
 
 // ---- FP64: the three-level form of Eq. (2)-(3) on (e^n, e^{n-1}) -----------
-// One block: the 32 x 8 node column (tx, ty) over the z planes of chunk kc.
+// One block: the TX x TY node column (tx, ty) over the z planes of chunk kc.
 // Per plane: stage e plane k+1, update the own edges of the nodes of plane
 // k from their stored coefficients, and gather the Joule power of e^n at the
 // node from its six incident edges.  Plane k + 2 and the node inputs of plane
@@ -442,9 +442,10 @@ __device__ __forceinline__ void st_plane(T *base, int64_t o, uint32_t n, uint32_
 // first; 16 x 16 rows are too short: 109).  With the node inputs read where
 // they are used, masks, and two barriers around a three-plane ring it took 162
 // and 1137 us.
-template <typename T, bool NT>
+template <typename T, int TX, int TY, bool NT>
 __device__ __forceinline__ void em_march_tile(const EmLaunch &L, const EmPtrs<T> &p, int64_t step, int tx, int ty,
-                                              int kc, int kchunk, int acc_joule, MarchSmem<T> &S) {
+                                              int kc, int kchunk, int acc_joule, MarchSmem<T, TX, TY> &S) {
+  constexpr int TXH = TX + 2, TYH = TY + 2;  // staged tile with halo
   const DevGrid &g = L.g;
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const uint32_t sy = uint32_t(g.sy), sz = uint32_t(g.sz);
@@ -455,7 +456,7 @@ __device__ __forceinline__ void em_march_tile(const EmLaunch &L, const EmPtrs<T>
   const int i0 = tx * TX, j0 = ty * TY;
   const int i = i0 + lx, j = j0 + ly;
   const int k0 = kc * kchunk, k1 = min(k0 + kchunk, nz + 1);
-  // per-thread x / y factors (clamped indices; masks select the valid terms)
+  // per-thread x / y factors (clamped indices)
   const bool active = i <= nx && j <= ny;
   const int ic = min(i, nx), jc = min(j, ny);
   if (tid < TX) {
@@ -1256,15 +1257,40 @@ __device__ __forceinline__ void em_march_tile_yee(const EmLaunch &L, const EmPtr
   step_plane(k, std::integral_constant<int, 0>{});
 }
 
-// MARCH: the FP64 march, the mixed runs or tiles, or whichever mixed one the
-// mesh takes.  NT: data used once goes past the caches (FP64, tiles).
-enum { kMarchFp64, kMarchRuns, kMarchTiles, kMarchMixed };
+// Which of the two FP64 tiles a mesh takes.  32 x 8 reads the smaller halo; 64 x 4
+// leaves fewer lanes idle where the rows of nodes are few, and is taken where
+// that makes its blocks a fifth fewer, unless all blocks find a CU of their own
+// anyway (chunks of one plane).  us per step, 32 x 8 | 64 x 4:
+//   4001x2x61 nodes 27.6 | 16.1   1001x4x401 42.7 | 33.1   97x4x1501 22.9 | 16.7
+//   501x9x443 56.7 | 42.3   501x12x332 46.9 | 41.0 (blocks 0.75 of the others')
+//   501x17x234 45.3 | 43.1   501x20x59 16.1 | 16.8 (0.83)   64x4x64 5.2 | 5.6 (128 blocks)
+__host__ __device__ inline bool em_flat(const DevGrid &g) {
+  const int64_t tile = int64_t((g.nx + kTileX) / kTileX) * ((g.ny + kTileY) / kTileY),
+                flat = int64_t((g.nx + kFlatX) / kFlatX) * ((g.ny + kFlatY) / kFlatY);
+  return flat * 5 <= tile * 4 && tile * (g.nz + 1) > 256;
+}
+
+// MARCH: the FP64 march in 32 x 8 or 64 x 4 tiles, the mixed runs or tiles, or
+// whichever of a precision's two the mesh takes.  NT: data used once goes past
+// the caches (FP64, mixed tiles).
+enum { kMarchFp64, kMarchRuns, kMarchTiles, kMarchMixed, kMarchFp64Flat, kMarchFp64Any };
 template <typename T, int MARCH, bool NT>
 __device__ __forceinline__ void march_tile(const EmLaunch &L, const EmPtrs<T> &p, int64_t step, int tx, int ty, int kc,
                                            int kchunk, int acc_joule) {
+  using Tile = MarchSmem<T, kTileX, kTileY>;
+  using Flat = MarchSmem<T, kFlatX, kFlatY>;
   if constexpr (MARCH == kMarchFp64) {
-    __shared__ MarchSmem<T> S;
-    em_march_tile<T, NT>(L, p, step, tx, ty, kc, kchunk, acc_joule, S);
+    __shared__ Tile S;
+    em_march_tile<T, kTileX, kTileY, NT>(L, p, step, tx, ty, kc, kchunk, acc_joule, S);
+  } else if constexpr (MARCH == kMarchFp64Flat) {
+    __shared__ Flat S;
+    em_march_tile<T, kFlatX, kFlatY, NT>(L, p, step, tx, ty, kc, kchunk, acc_joule, S);
+  } else if constexpr (MARCH == kMarchFp64Any) {
+    __shared__ __align__(16) char S[std::max(sizeof(Tile), sizeof(Flat))];
+    if (em_flat(L.g))
+      em_march_tile<T, kFlatX, kFlatY, NT>(L, p, step, tx, ty, kc, kchunk, acc_joule, *reinterpret_cast<Flat *>(S));
+    else
+      em_march_tile<T, kTileX, kTileY, NT>(L, p, step, tx, ty, kc, kchunk, acc_joule, *reinterpret_cast<Tile *>(S));
   } else if constexpr (MARCH == kMarchRuns) {
     __shared__ YeeSmem S;
     em_march_run_yee(L, p, step, tx, kc, kchunk, acc_joule, S);
@@ -1879,9 +1905,9 @@ void em_tiles(const DevGrid &g, int precision, int kchunk, int *ntx, int *nty, i
     *ntx = (g.nx + 1 + MX - 1) / MX;
     *nty = (g.ny + 1 + MY - 1) / MY;
   } else {
-    // TX x TY node tiles
-    *ntx = (g.nx + 1 + TX - 1) / TX;
-    *nty = (g.ny + 1 + TY - 1) / TY;
+    const int tx = em_flat(g) ? kFlatX : kTileX, ty = em_flat(g) ? kFlatY : kTileY;
+    *ntx = (g.nx + 1 + tx - 1) / tx;
+    *nty = (g.ny + 1 + ty - 1) / ty;
   }
   *nkc = (g.nz + 1 + kchunk - 1) / kchunk;
 }
@@ -1931,12 +1957,13 @@ hipError_t launch_em_step(const EmLaunch &L, hipStream_t s) {
   const dim3 block(BX, BY, 1);
   if (L.precision == ETM_PREC_FP64) {
     EmPtrs<double> p{(const double *)L.e0[0], (const double *)L.e1[0], (double *)L.out0[0], nullptr};
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nb), block, 0, s, L, p, ntx, nty, nkc, kc, L.acc_joule);
+    };
     if (em_streams(L.g.ntot, true))
-      hipLaunchKernelGGL((em_march_kernel<double, kMarchFp64, true>), dim3(nb), block, 0, s, L, p, ntx, nty, nkc, kc,
-                         L.acc_joule);
+      launch(em_flat(L.g) ? em_march_kernel<double, kMarchFp64Flat, true> : em_march_kernel<double, kMarchFp64, true>);
     else
-      hipLaunchKernelGGL((em_march_kernel<double, kMarchFp64, false>), dim3(nb), block, 0, s, L, p, ntx, nty, nkc, kc,
-                         L.acc_joule);
+      launch(em_flat(L.g) ? em_march_kernel<double, kMarchFp64Flat, false> : em_march_kernel<double, kMarchFp64, false>);
   } else {
     EmPtrs<float> p{(const float *)L.e0[0], (const float *)L.e1[0], (float *)L.out0[0], (float *)L.out1[0]};
     if (em_runs(L.g))
@@ -1982,8 +2009,9 @@ hipError_t launch_em_pair_schedule(const EmLaunch &La, const EmLaunch &Lb, int n
     if (La.precision == ETM_PREC_FP64) {
       EmPtrs<double> pa{(const double *)La.e0[0], (const double *)La.e1[0], (double *)La.out0[0], nullptr};
       EmPtrs<double> pb{(const double *)Lb.e0[0], (const double *)Lb.e1[0], (double *)Lb.out0[0], nullptr};
-      hipLaunchKernelGGL((em_march_pair_kernel<double, kMarchFp64>), dim3(nb), block, 0, s, La, pa, pb, ntx, nty, kcA, nkcA,
-                         kcB, nkcB, kc, La.acc_joule);
+      const auto kernel =
+          em_flat(La.g) ? em_march_pair_kernel<double, kMarchFp64Flat> : em_march_pair_kernel<double, kMarchFp64>;
+      hipLaunchKernelGGL(kernel, dim3(nb), block, 0, s, La, pa, pb, ntx, nty, kcA, nkcA, kcB, nkcB, kc, La.acc_joule);
     } else {
       EmPtrs<float> pa{(const float *)La.e0[0], (const float *)La.e1[0], (float *)La.out0[0], (float *)La.out1[0]};
       EmPtrs<float> pb{(const float *)Lb.e0[0], (const float *)Lb.e1[0], (float *)Lb.out0[0], (float *)Lb.out1[0]};
@@ -1996,19 +2024,21 @@ hipError_t launch_em_pair_schedule(const EmLaunch &La, const EmLaunch &Lb, int n
   return hipSuccess;
 }
 
+bool em_tile_is_flat(const DevGrid &g) { return em_flat(g); }
+
 hipError_t launch_em_batched(const BatchVar *vars, const int4 *items, int n_items, int64_t s, int precision,
-                             int64_t nodes, hipStream_t st) {
+                             int64_t nodes, bool any_flat, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  const dim3 grid(n_items), block(BX, BY);
   const bool nt = em_streams(nodes, precision == ETM_PREC_FP64);
-  if (precision == ETM_PREC_FP64 && nt)
-    hipLaunchKernelGGL((em_march_batched<double, kMarchFp64, true>), grid, block, 0, st, vars, items, n_items, s);
-  else if (precision == ETM_PREC_FP64)
-    hipLaunchKernelGGL((em_march_batched<double, kMarchFp64, false>), grid, block, 0, st, vars, items, n_items, s);
-  else if (nt)
-    hipLaunchKernelGGL((em_march_batched<float, kMarchMixed, true>), grid, block, 0, st, vars, items, n_items, s);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(n_items), dim3(BX, BY), 0, st, vars, items, n_items, s);
+  };
+  if (precision != ETM_PREC_FP64)
+    launch(nt ? em_march_batched<float, kMarchMixed, true> : em_march_batched<float, kMarchMixed, false>);
+  else if (any_flat)  // (the kernel of both tiles is 1 to 3 % slower on batches of ordinary meshes)
+    launch(nt ? em_march_batched<double, kMarchFp64Any, true> : em_march_batched<double, kMarchFp64Any, false>);
   else
-    hipLaunchKernelGGL((em_march_batched<float, kMarchMixed, false>), grid, block, 0, st, vars, items, n_items, s);
+    launch(nt ? em_march_batched<double, kMarchFp64, true> : em_march_batched<double, kMarchFp64, false>);
   return hipGetLastError();
 }
 

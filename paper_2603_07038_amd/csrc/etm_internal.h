@@ -205,9 +205,11 @@ struct BatchVar {
   int64_t step0;          // plan step at the start of the advance call
   int cur0, th0, R, kchunk, acc_joule0, pad1;
 };
-// Step `offset` counted from the descriptors' step0; nodes: of all variants.
+// Step `offset` counted from the descriptors' step0; nodes: of all variants;
+// any_flat: some FP64 variant has the 64 x 4 tile (em_tile_is_flat).
 hipError_t launch_em_batched(const BatchVar *vars, const int4 *items, int n_items, int64_t offset, int precision,
-                             int64_t nodes, hipStream_t s);
+                             int64_t nodes, bool any_flat, hipStream_t s);
+bool em_tile_is_flat(const DevGrid &g);
 
 struct ThermalLaunch {
   DevGrid g;

@@ -3,6 +3,8 @@
 // test_launch_rules.py.  Linked with the library; nothing is launched.
 //   partials PREC NX NY NZ -> rows the solve's partials hold, and the blocks of
 //                             the HEX8 operator in FP32 and FP64
+//   tiles PREC NX NY NZ    -> blocks along x and y and z-chunks of one plane of
+//                             the march on its own
 #include <cstdio>
 #include <string>
 #include <vector>
@@ -39,6 +41,13 @@ int main() {
       std::printf("%lld %lld %lld\n", (long long)(p->r_partm.bytes / (kRedWidth * 8)),
                   (long long)mech::cell_blocks<float>(g), (long long)mech::cell_blocks<double>(g));
       etm_plan_destroy(p);
+    } else if (std::string(what) == "tiles") {
+      g.sy = (nx + 1 + kPad - 1) / kPad * kPad;
+      g.sz = g.sy * (ny + 1);
+      g.ntot = g.sz * (nz + 1);
+      int ntx, nty, nkc;
+      em_tiles(g, prec, 1, &ntx, &nty, &nkc);
+      std::printf("%d %d %d\n", ntx, nty, nkc);
     } else {
       std::printf("error unknown query\n");
     }

@@ -196,3 +196,43 @@ def test_coefficient_refresh_matches_full(shape, precision):
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
     assert np.abs(out[0][3]).max() > 0
+
+
+# FP64 meshes of few rows of nodes take tiles of 64 x 4 (above 256 blocks): the
+# tile's edges, one to nine rows, and a launch whose one-time data bypasses the
+# caches; slabs, and a batch together with a mesh of 32 x 8 tiles.
+@pytest.mark.parametrize("shape", [(62, 1, 150), (63, 3, 140), (64, 2, 140), (127, 8, 40), (129, 3, 70), (2000, 3, 300)])
+def test_fp64_flat_tiles_do_not_change_results(shape):
+    prob = W.random_problem(sum(shape), *shape, n_steps=8, R=4, n_ports=6, amp=3e10, em_bc=(1, 0, 0, 0, 1, 0))
+    other = W.random_problem(7, 33, 20, 12, n_steps=8, R=4, n_ports=4, amp=3e10)
+    dt = etm.cfl_dt(prob)
+    J = prob.sample_J_half(dt, 8)
+    out = []
+    for form in ("solo", "slabs", "batch"):
+        plan = etm.Plan(prob, J, dt=dt, precision=etm.ETM_PREC_FP64, n_steps=8, history=False,
+                        em_slabs=2 if form == "slabs" else 0)
+        if form == "batch":
+            second = etm.Plan(other, other.sample_J_half(etm.cfl_dt(other), 8), precision=etm.ETM_PREC_FP64, n_steps=8,
+                              history=False)
+            batch = etm.Batch(2)
+            batch.attach(plan)
+            batch.attach(second)
+            batch.advance(8)
+            alone = etm.Plan(other, other.sample_J_half(etm.cfl_dt(other), 8), precision=etm.ETM_PREC_FP64, n_steps=8,
+                             history=False)
+            alone.advance(8)
+            for a, b in zip(alone.e(), second.e()):
+                np.testing.assert_array_equal(a, b)
+        else:
+            plan.advance(8)
+        plan.sync()
+        out.append(plan.e() + plan.e_prev() + [plan.read(etm.ETM_FIELD_THETA)])
+    for form in out[1:]:
+        for a, b in zip(out[0], form):
+            np.testing.assert_array_equal(a, b)
+    assert max(np.abs(x).max() for x in out[0][:3]) > 0
+    st, _ = oracle.Oracle(prob).run(dt, 8, J, stride=0, probes=None)
+    scale = max(np.abs(x).max() for x in st["e"])
+    for g, w in zip(out[0][:3], st["e"]):
+        assert np.abs(g - w).max() <= 1e-9 * scale
+    assert rel_err(out[0][6], st["theta"]) <= 1e-9

@@ -41,3 +41,14 @@ def test_solver_partials_hold_every_block(ask, precision):
               (256, 256, 64)]
     for shape, (rows, fp32, fp64) in zip(shapes, ask(["partials %d %d %d %d" % (precision, *s) for s in shapes])):
         assert rows >= max(fp32, fp64), (shape, rows, fp32, fp64)
+
+
+# An FP64 block is 256 nodes of a plane: 32 x 8, or 64 x 4 where that takes at
+# least a fifth fewer blocks and the launch has more of them than CUs.
+def test_fp64_tiles_do_not_idle_on_few_rows(ask):
+    shapes = [(nx, ny, nz) for nx in (1, 30, 31, 32, 63, 64, 96, 500, 4000) for ny in (1, 2, 3, 4, 7, 8, 11, 12, 15, 16, 63, 255)
+              for nz in (1, 60, 400)]
+    for (nx, ny, nz), (tx, ty, kc) in zip(shapes, ask(["tiles %d %d %d %d" % (etm.ETM_PREC_FP64, *s) for s in shapes])):
+        tile, flat = -(-(nx + 1) // 32) * -(-(ny + 1) // 8), -(-(nx + 1) // 64) * -(-(ny + 1) // 4)
+        want = flat if 5 * flat <= 4 * tile and tile * (nz + 1) > 256 else tile
+        assert kc == nz + 1 and tx * ty == want, (nx, ny, nz, tx, ty)
