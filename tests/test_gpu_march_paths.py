@@ -236,3 +236,93 @@ def test_fp64_flat_tiles_do_not_change_results(shape):
     for g, w in zip(out[0][:3], st["e"]):
         assert np.abs(g - w).max() <= 1e-9 * scale
     assert rel_err(out[0][6], st["theta"]) <= 1e-9
+
+
+# A mixed plan just below the size from which it takes the tiles, just above, and
+# above it with a plane that tiles pad by more than 30 % (runs): as it is, in
+# runs and in tiles (forced through a batch's table).
+@pytest.mark.parametrize("shape", [(254, 188, 64), (254, 189, 64), (129, 190, 150)])
+def test_mixed_plans_either_side_of_the_streaming_size(shape):
+    prob = W.random_problem(sum(shape), *shape, n_steps=8, R=4, n_ports=6, amp=3e10)
+    dt = etm.cfl_dt(prob)
+    J = prob.sample_J_half(dt, 8)
+    cls = str(int(np.floor(np.log2(shape[0] * shape[1] * shape[2]))))
+    out = []
+    for layout in (None, 1, 2):
+        plan = etm.Plan(prob, J, dt=dt, precision=etm.ETM_PREC_MIXED, n_steps=8, history=False)
+        if layout:
+            batch = etm.Batch(1, json.dumps({"layout": {cls: layout}}))
+            batch.attach(plan)
+            batch.advance(8)
+        else:
+            plan.advance(8)
+        plan.sync()
+        out.append(plan.e() + [plan.read(etm.ETM_FIELD_THETA)])
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            np.testing.assert_array_equal(a, b)
+    assert np.abs(out[0][0]).max() > 0
+
+
+# A mixed batch whose nodes stream, in tiles of odd chunks and as the default
+# table has it, with a variant that streams by itself and small ones.
+@pytest.mark.parametrize("table", ["tiles", "default"])
+def test_mixed_batch_above_the_streaming_size_matches_solo(table):
+    shapes = [(131, 118, 45), (70, 9, 33), (260, 190, 66), (121, 120, 50), (64, 64, 40), (63, 3, 17)]
+    probs = [W.random_problem(q, *s, n_steps=8, R=4, n_ports=4, amp=3e10) for q, s in enumerate(shapes)]
+    assert sum((p.nx + 1) * (p.ny + 1) * (p.nz + 1) for p in probs) * 85 > 1 << 28
+    plans = []
+    for _ in range(2):
+        plans.append([etm.Plan(p, p.sample_J_half(etm.cfl_dt(p), 8), precision=etm.ETM_PREC_MIXED, n_steps=8,
+                               history=False) for p in probs])
+    classes = {int(np.floor(np.log2(p.n_cells))) for p in probs}
+    tune = {"kchunk": {str(c): [3, 5, 7][c % 3] for c in classes}, "layout": {str(c): 2 for c in classes}}
+    batch = etm.Batch(len(probs), json.dumps(tune) if table == "tiles" else None)
+    for p in plans[0]:
+        batch.attach(p)
+    batch.advance(8)
+    for a, b in zip(*plans):
+        a.sync()
+        b.advance(8)
+        b.sync()
+        for x, y in zip(a.e() + a.e_prev() + [a.read(etm.ETM_FIELD_THETA)],
+                        b.e() + b.e_prev() + [b.read(etm.ETM_FIELD_THETA)]):
+            np.testing.assert_array_equal(x, y)
+
+
+# The thermal kernel over chunks of 8 and of 12 planes (700 blocks or more),
+# against the oracle, as in test_thermal_columns.
+@pytest.mark.parametrize("precision", [etm.ETM_PREC_FP64, etm.ETM_PREC_MIXED])
+@pytest.mark.parametrize("shape", [(127, 255, 47), (126, 253, 65)])
+def test_thermal_long_chunks(shape, precision):
+    prob = W.random_problem(sum(shape), *shape, n_steps=3, R=1, n_ports=4, amp=3e10)
+    o = oracle.Oracle(prob)
+    dt = o.cfl_dt()
+    J = prob.sample_J_half(dt, 3)
+    plan = etm.Plan(prob, J, dt=dt, precision=precision, n_steps=3, history=False)
+    plan.advance(3)
+    plan.sync()
+    st, _ = o.run(dt, 3, J, stride=0, probes=None)
+    assert rel_err(plan.read(etm.ETM_FIELD_THETA), st["theta"]) <= (1e-9 if precision == etm.ETM_PREC_FP64 else 1e-6)
+
+
+# The refresh over chunks of 8 planes (4800 blocks or more), the last one short,
+# against the full one at a restore, as in test_coefficient_refresh_matches_full.
+@pytest.mark.parametrize("precision", [etm.ETM_PREC_FP64, etm.ETM_PREC_MIXED])
+def test_coefficient_refresh_long_chunks(precision):
+    prob = W.random_problem(9, 254, 1199, 30, n_steps=8, R=2, n_ports=4, amp=3e10)
+    dt = etm.cfl_dt(prob)
+    J = prob.sample_J_half(dt, 8)
+    plan = etm.Plan(prob, J, dt=dt, precision=precision, n_steps=8, history=False)
+    plan.advance(4)
+    plan.sync()
+    again = etm.Plan(prob, J, dt=dt, precision=precision, n_steps=8, history=False)
+    again.restore(plan.checkpoint())
+    out = []
+    for p in (plan, again):
+        p.advance(4)
+        p.sync()
+        out.append(p.e() + [p.read(etm.ETM_FIELD_THETA)])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    assert np.abs(out[0][3]).max() > 0

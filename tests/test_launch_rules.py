@@ -52,3 +52,21 @@ def test_fp64_tiles_do_not_idle_on_few_rows(ask):
         tile, flat = -(-(nx + 1) // 32) * -(-(ny + 1) // 8), -(-(nx + 1) // 64) * -(-(ny + 1) // 4)
         want = flat if 5 * flat <= 4 * tile and tile * (nz + 1) > 256 else tile
         assert kc == nz + 1 and tx * ty == want, (nx, ny, nz, tx, ty)
+
+
+# A mixed plan takes tiles of 64 x 4 nodes when a step's 85 bytes per node (rows
+# padded to 16) exceed 256 MB and the tiles pad the plane by at most 30 %, and
+# runs of 248 nodes of the plane otherwise: either side of both lines.
+def test_mixed_form_switches_where_a_step_streams(ask):
+    shapes = [(254, 188, 64), (254, 189, 64), (254, 190, 64), (255, 188, 64), (255, 190, 64), (256, 190, 64), (129, 190, 150),
+              (127, 190, 150), (207, 255, 64), (191, 255, 64), (61, 61, 38), (1023, 255, 12), (1024, 1024, 128)]
+    got = ask(["tiles %d %d %d %d" % (etm.ETM_PREC_MIXED, *s) for s in shapes])
+    forms = []
+    for (nx, ny, nz), (tx, ty, kc) in zip(shapes, got):
+        nodes = -(-(nx + 1) // 16) * 16 * (ny + 1) * (nz + 1)
+        bx, by = -(-(nx + 1) // 64), -(-(ny + 1) // 4)
+        tiles = nodes * 85 > 1 << 28 and bx * by * 256 * 10 <= (nx + 1) * (ny + 1) * 13
+        want = (bx, by) if tiles else (-(-(nx + 1) * (ny + 1) // 248), 1)
+        assert (tx, ty) == want and kc == nz + 1, (nx, ny, nz, tx, ty)
+        forms.append(tiles)
+    assert forms[:3] == [False, True, True] and not forms[6] and forms[7]
