@@ -253,7 +253,12 @@ __global__ __launch_bounds__(256) void wave_sample_kernel(const double *aw, int 
   Ja[id] = wave_value(aw + w * kWaveStride, (double(base + q) - 0.5) * dt);
 }
 
-// Entry of a port edge in the place of its eps_r among the coefficients.
+// Entry of a port edge in the place of its eps_r among the coefficients.  The
+// marches index DevPorts::rec and er with what they find there and check only
+// the node's port flag, so every slot of a flagged edge has to hold an entry:
+// flags and entries come from one list at plan creation, only the full refresh
+// writes these slots, and it runs at bind and at restore, before any march.  A
+// kernel that changes eps_r of a port edge has to write DevPorts::er instead.
 __device__ __forceinline__ float port_code(int q, float) { return __int_as_float(q); }
 __device__ __forceinline__ double port_code(int q, double) { return __longlong_as_double(q); }
 __device__ __forceinline__ int port_entry(float c) { return __float_as_int(c); }
@@ -356,8 +361,9 @@ struct EmPtrs {
 };
 
 // Joule power density at node n from the stored coefficients of its six
-// incident edges and their field values v (own x, y, z, low x, y, z).  The
-// same code serves the march kernel and the flush / thermal kernels.
+// incident edges and their field values v (own x, y, z, low x, y, z).  For the
+// flush kernel; the marches and the thermal kernel hold these values already
+// and form the same six products in the same order.
 // The mixed path stores 2a, so its conductances are halved (exactly) here.
 template <typename T>
 __device__ __forceinline__ double joule_from_coef(const T *cf, uint32_t cs, uint32_t n, uint32_t sy, uint32_t sz,
@@ -1453,7 +1459,8 @@ __device__ __forceinline__ double pending_joule(const DevGrid &g, const T *const
 // FULL: every node, with eps_r and the ports' entries (at bind and restore).
 // Otherwise the refresh after a temperature change: only edges next to a cell
 // whose sigma depends on it change, and eps_r never does.  One block: 64 x 4
-// nodes over up to 32 planes, whose flags it reads at once; planes without such
+// nodes over up to 8 planes (launch_coef; the mask of planes has room for 32),
+// whose flags it reads at once; planes without such
 // a node cost nothing more, and a block without one leaves before it loads the
 // material table.
 // Bound by the bytes of those nodes (about 80 each in mixed precision): 95 us
@@ -1921,26 +1928,32 @@ int64_t em_list_tiles(const DevGrid &g, int precision, int kchunk) {
 
 int em_kchunk(const DevGrid &g, int precision, bool alone) {
   // Planes per block: long chunks on many columns, short ones otherwise, and
-  // shorter still (down to 4) while a launch would have fewer than 2048 blocks
-  // to spread over the 256 CUs.  us per step at 4, 6, 11 and 17 planes: mixed
-  // 256x256x64 98.0, 94.0, 92.0, 97.1, 384x384x96 301, 297, 301, 309,
-  // 1024x1024x128 2588, 2558, 2546, 2585; FP64 256x256x64 101, 97.6, 94.7, 96.3,
-  // 384x384x96 345, 346, 354, 361.
+  // shorter still (down to 4) while there would be fewer than 2048 blocks to
+  // spread over the 256 CUs.  Blocks are those of em_list_tiles here (up to
+  // twice or half the launch's own), whose limit the chunk also decides.
+  // us per step at 4, 6, 11 and 17 planes: mixed
+  // 256x256x64 96.8, 94.3, 93.1, 97.7, 384x384x96 299, 296, 303, 313,
+  // 1024x1024x128 2592, 2569, 2557, 2604; FP64 256x256x64 98.7, 96.1, 94.5, 97.4,
+  // 384x384x96 332, 336, 345, 356.
   int64_t cols = em_list_tiles(g, precision, g.nz + 1);
   auto blocks = [&](int kc) { return cols * ((g.nz + 1 + kc - 1) / kc); };
   int kc = blocks(12) >= 8192 ? 12 : 6;
   while (kc > 4 && blocks(kc) < 2048) kc = std::max(4, kc - 2);
-  // A launch that has the GPU to itself and fits on it at once (1024 blocks
+  // A launch of one mesh that fits on the GPU at once (1024 blocks
   // at 4 waves per SIMD) lasts as long as one block: a chunk's planes are a
   // serial chain of 1.5 to 2 us each, so the shortest chunk that still fits is
-  // taken.  us per step in FP64 | mixed at chunks of 1, 2, 3, 4:
-  //   32x32x16    5.9  7.6  9.0 10.7 |  6.4  8.5 10.4 12.2
-  //   61x61x38    9.1  9.6 10.7 13.0 |  9.4 10.7 11.6 14.0
-  //   80x77x48   14.8 13.2 15.0 17.7 | 13.4 12.8 15.4 18.1
-  //   110x100x40 20.1 19.1 17.7 19.4 | 15.9 15.1 16.0 17.9
-  //   152x120x43 26.6 23.5 25.0 23.4 | 24.0 22.0 23.5 22.4
-  // (one generation from chunks 1, 1, 2, 3 | 2 and 4 on).  Larger meshes keep
-  // the rule above: 192x192x48 takes 46.3 | 42.1 at 4, 46.7 | 42.1 at 2.
+  // taken.  It is taken too where other plans march at the same time on streams
+  // of their own: us per step and plan at chunks of 4 | the shortest, mixed, two
+  // plans of 32x32x16 5.1 | 4.6, 61x61x38 6.1 | 5.5, 110x100x40 8.8 | 8.8, four
+  // plans 5.3 | 4.4, 6.0 | 5.9, 9.2 | 9.3.  One plan, us per step in FP64 | mixed
+  // at chunks of 1, 2, 3, 4:
+  //   32x32x16    5.7  7.3  8.4  9.5 |  5.4  7.3  8.8 10.1
+  //   61x61x38    9.1  9.0 10.4 12.2 |  8.6  9.2 10.4 12.7
+  //   80x77x48   13.1 12.8 13.7 16.5 | 11.1 11.2 13.4 15.8
+  //   110x100x40 16.5 15.3 16.6 18.1 | 14.4 13.3 13.6 15.6
+  //   152x120x43 25.2 21.9 22.1 21.6 | 22.0 19.2 19.2 19.9
+  // (one generation from chunks 1, 1, 2, 3, 4 | 1, 1, 2, 2, 4 on).  Larger meshes
+  // keep the rule above: 192x192x48 takes 42.7 | 34.9 at 4, 44.8 | 36.7 at 2.
   int ntx, nty, nkc;
   em_tiles(g, precision, 1, &ntx, &nty, &nkc);
   cols = int64_t(ntx) * nty;

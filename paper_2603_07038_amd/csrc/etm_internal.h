@@ -78,7 +78,8 @@ struct PortRec {
 // Port edges, sorted by key = dir * ntot + node.  The march finds the entry
 // of a port edge without a search: the coefficient kernel writes the entry's
 // number, as bits, in the place of the edge's eps_r (which the march takes
-// from er), so it arrives with the coefficients of the plane.
+// from er), so it arrives with the coefficients of the plane.  Nothing checks
+// that number: see port_entry in em.hip for who may write it.
 struct DevPorts {
   int n_edges;
   const int64_t *key;

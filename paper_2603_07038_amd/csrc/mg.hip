@@ -600,9 +600,9 @@ __global__ __launch_bounds__(256) void mg_stencil_kernel(MgLevel<T> L, V3<T> x, 
     const int64_t N = L.n, n = int64_t(k) * L.sz + int64_t(j) * L.sy + i;
     const typename Op::Pre pre = op.load(n);
     T y[3] = {T(0), T(0), T(0)};
-    // the centre first, then kPair offsets and their opposites per round trip
-    // to memory (2: 77 us against 79, but 84 registers; 3: 82)
-    constexpr int kPair = 1;
+    // the centre first, then an offset and its opposite per round trip to memory
+    // (two pairs: 77 us against 79 on the 129x129x33 level, but 84 registers;
+    // three: 82)
     {
       T R[9], xv[3];
 #pragma unroll
@@ -613,40 +613,35 @@ __global__ __launch_bounds__(256) void mg_stencil_kernel(MgLevel<T> L, V3<T> x, 
       for (int c = 0; c < 3; ++c) y[c] = R[3 * c] * xv[0] + R[3 * c + 1] * xv[1] + R[3 * c + 2] * xv[2];
     }
 #pragma unroll 1
-    for (int q0 = 1; q0 < kMgUpper; q0 += kPair) {
-      T R[kPair][2][9], xv[kPair][2][3];
-      bool use[kPair][2];
+    for (int q = 1; q < kMgUpper; ++q) {
+      T R[2][9], xv[2][3];
+      bool use[2];
+      const int o = 13 + q;
+      const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
 #pragma unroll
-      for (int s = 0; s < kPair; ++s) {
-        const int q = min(q0 + s, kMgUpper - 1), o = 13 + q;
-        const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
+      for (int h = 0; h < 2; ++h) {
+        const int dx = h ? -ox : ox, dy = h ? -oy : oy, dz = h ? -oz : oz;
+        const int ii = i + dx, jj = j + dy, kk = k + dz;
+        use[h] = ii >= 0 && ii <= L.nx && jj >= 0 && jj <= L.ny && kk >= 0 && kk <= L.nz;
+        const int64_t m = use[h] ? n + dx + dy * L.sy + dz * L.sz : n;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int dx = h ? -ox : ox, dy = h ? -oy : oy, dz = h ? -oz : oz;
-          const int ii = i + dx, jj = j + dy, kk = k + dz;
-          use[s][h] = q0 + s < kMgUpper && ii >= 0 && ii <= L.nx && jj >= 0 && jj <= L.ny && kk >= 0 && kk <= L.nz;
-          const int64_t m = use[s][h] ? n + dx + dy * L.sy + dz * L.sz : n;
+        for (int c = 0; c < 3; ++c) xv[h][c] = x.c[c][m];
+        const int64_t p = h ? m : n;
 #pragma unroll
-          for (int c = 0; c < 3; ++c) xv[s][h][c] = x.c[c][m];
-          const int64_t p = h ? m : n;
-#pragma unroll
-          for (int e = 0; e < 9; ++e) R[s][h][e] = L.A[stencil_idx(q, e / 3, e % 3, N, p)];
-        }
+        for (int e = 0; e < 9; ++e) R[h][e] = L.A[stencil_idx(q, e / 3, e % 3, N, p)];
       }
 #pragma unroll
-      for (int s = 0; s < kPair; ++s)
+      for (int h = 0; h < 2; ++h) {
+        T xm[3];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          T xm[3];
+        for (int c = 0; c < 3; ++c) xm[c] = use[h] ? xv[h][c] : T(0);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) xm[c] = use[s][h] ? xv[s][h][c] : T(0);
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const T *B = R[s][h];
-            y[c] += h ? B[c] * xm[0] + B[3 + c] * xm[1] + B[6 + c] * xm[2]
-                      : B[3 * c] * xm[0] + B[3 * c + 1] * xm[1] + B[3 * c + 2] * xm[2];
-          }
+        for (int c = 0; c < 3; ++c) {
+          const T *B = R[h];
+          y[c] += h ? B[c] * xm[0] + B[3 + c] * xm[1] + B[6 + c] * xm[2]
+                    : B[3 * c] * xm[0] + B[3 * c + 1] * xm[1] + B[3 * c + 2] * xm[2];
         }
+      }
     }
     op(n, y, pre, red);
   }
