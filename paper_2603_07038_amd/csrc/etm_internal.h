@@ -349,7 +349,8 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 // 101 | 96, mixed 1025x1025x129 2754 | 2590; groups of 32 to 256 are within
 // 2 %, 1024 loses 2 to 5 %.  (FP64 153x121x44, which fits: 22.2 | 24.1.)
 // A CG iteration, whose operator and level-0 smoothing walk blocks this way:
-// 513x513x65 nodes 4480 | 4375 mixed, 8358 | 8249 FP64.
+// 513x513x65 nodes 4480 | 4375 mixed, 8358 | 8249 FP64 (smoothing steps that
+// stored no direction).
 __device__ __forceinline__ int grouped_block(int b, int nb) {
   if (nb <= 1024) return xcd_remap(b, nb);
   const int g0 = b / 128 * 128;

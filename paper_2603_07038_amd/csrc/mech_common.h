@@ -198,12 +198,13 @@ __device__ __forceinline__ void st(T *p, int64_t n, T v) { p[n] = v; }
 // leaves the column's result on plane ck, the layer's bottom plus the top of
 // the layer below, in the other half of the LDS buffer.
 // Bound by VALU issue (about 300 instructions per wave and layer) together
-// with HBM: on 257x257x65 nodes in FP32 the plain residual takes 57 us (194 MB
-// of counted traffic, 3.4 TB/s), the smoothing step 99 us (416 MB, 4.2 TB/s).
+// with HBM: on 257x257x65 nodes in FP32 the plain residual takes 56 us (179 MB
+// of counted traffic, 3.2 TB/s), a smoothing step 84 us (350 MB, 4.2 TB/s), or
+// 96 us (392 MB) where it stores its direction.
 // A form that transformed each cell's eight corners by itself and left 24
 // results per cell in LDS (two barriers a layer, every load masked where it
-// was issued) took 84 and 110 us; in FP64 on 98x84x34 nodes 19.1 and 21.2 us
-// against 14.4 and 16.6 us now.
+// was issued) took 84 and (every step storing a direction) 110 us; in FP64 on
+// 98x84x34 nodes 19.1 and 21.2 us against 14.6 and 16.9 us now.
 // Fixed DOFs give zero rows; x is taken as zero on them.  The Lame constants
 // come from a per-block LDS copy of the material table (both zero for a void
 // material and outside the mesh).  The epilogue sees (n, y, x at the node,
@@ -221,9 +222,9 @@ inline dim3 cell_grid(const DevGrid &g, int kchunk) {
 // the reduction's partials always hold (one per block: max(1024, node blocks));
 // a mesh whose tiles alone are more takes one chunk, and a plan gives its
 // partials a row for each (mech_part_rows).  On
-// 257x257x65 nodes in FP32 that is 22 planes: 57.6 us for the residual and
-// 99.5 us for the smoothing step, against 70.6 and 105.9 us at 5 planes; on
-// 161x153x49 nodes 7 planes, 21.2 and 25.5 us against 24.1 and 29.3 us at 4.
+// 257x257x65 nodes in FP32 that is 22 planes: 55 us for the residual and
+// 85 us for a smoothing step, against 69 and 98 us at 5 planes; on
+// 161x153x49 nodes 7 planes, 21.6 and 24.8 us against 25.2 and 29.2 us at 4.
 template <typename T>
 inline int cell_kchunk(const DevGrid &g) {
   const int64_t tiles = int64_t((g.nx + 1 + CX - 2) / (CX - 1)) * ((g.ny + 1 + CY - 2) / (CY - 1));

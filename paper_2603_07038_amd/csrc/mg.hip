@@ -480,14 +480,16 @@ __device__ __forceinline__ void dinv_apply(const T D[6], const T r[3], T z[3]) {
 }
 
 // A Chebyshev step is x_{k+1} = x_k + d_{k+1}, d_{k+1} = c1 d_k + c2 Dinv (b - A x_k).
-// The direction d is a vector of its own where a later step needs it.  A step
-// from x = 0 has d = x, so of the four steps of a cycle at the usual degree of 2
-// only the first after the coarse correction stores a direction, and the one
-// that reads it, the last, writes its result over it: a node reads its own entry
-// before it writes.  (Formed again as x_k - x_{k-1}, d is rounded like x and not
+// The direction d is a vector of its own where a later step needs it: a step that
+// another follows stores it (74 B per level-0 node in FP32, 86 if it also reads
+// one), and the last one only reads it (74 B) and writes its result over it, as a
+// node reads its own entry before it writes.  A step from x = 0 has d = x.  Of
+// the five steps of a cycle after the first, at the usual degree of 3 on level 0,
+// three store a direction, and one of three on the other levels (degree 2).
+// (Formed again as x_k - x_{k-1}, d needs no store but is rounded like x and not
 // like itself: errors of thirty mixed solves of packages 2 % larger in the mean.
-// It needs no store: us per CG iteration 1188 | 1267 mixed and 2226 | 2311 FP64
-// on 257x257x65 nodes, 431 | 452 and 733 | 764 on 161x153x49.)
+// us per CG iteration that way | with d stored: 1188 | 1267 mixed and 2226 | 2311
+// FP64 on 257x257x65 nodes, 431 | 452 and 733 | 764 on 161x153x49.)
 enum { kDirNone = 0, kDirX = 1, kDirKept = 2 };  // d_k: none (c1 = 0), x itself, stored
 
 // First Chebyshev step from x = 0 at node n (a node index or a NodeAt):
@@ -776,7 +778,7 @@ __global__ __launch_bounds__(192) void mg_restrict_kernel(MgLevel<T> F, V3<T> r,
 // x_F += P x_C on the live DOFs of F.  A thread takes one (i, j) up kProlong
 // fine planes: the four coarse columns around it are interpolated in the
 // plane once per coarse plane, for the two fine planes that use it.  Bound by
-// HBM (x read and written): 28 us on 257x257x65 nodes in FP32, 50 us with a
+// HBM (x read and written): 30 us on 257x257x65 nodes in FP32, 50 us with a
 // thread per node reading its eight corners.
 constexpr int kProlong = 4;
 template <typename T>
