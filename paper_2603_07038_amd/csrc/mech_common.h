@@ -232,8 +232,12 @@ inline int cell_kchunk(const DevGrid &g) {
   const int64_t rows = std::max<int64_t>(1024, int64_t(nb.x) * nb.y * nb.z), resident = sizeof(T) == 4 ? 1024 : 512;
   int best = g.nz + 1;
   int64_t least = INT64_MAX;
+  // from one chunk of all planes on, each number of chunks at its shortest (a
+  // longer one costs more): some 2 sqrt(nz) candidates, as this runs at every launch
   for (int kc = g.nz + 1; kc >= 2; --kc) {
-    const int64_t blocks = tiles * ((g.nz + 1 + kc - 1) / kc);
+    const int chunks = (g.nz + 1 + kc - 1) / kc;
+    kc = (g.nz + 1 + chunks - 1) / chunks;
+    const int64_t blocks = tiles * chunks;
     if (blocks > rows && kc <= g.nz) break;
     const int64_t cost = (blocks + resident - 1) / resident * (kc + 2);
     if (cost < least) {

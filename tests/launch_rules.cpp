@@ -5,6 +5,9 @@
 //                             the HEX8 operator in FP32 and FP64
 //   tiles PREC NX NY NZ    -> blocks along x and y and z-chunks of one plane of
 //                             the march on its own
+//   chunk PREC NX NY NZ    -> planes per block of the HEX8 operator, and the
+//                             nanoseconds that choosing them takes
+#include <chrono>
 #include <cstdio>
 #include <string>
 #include <vector>
@@ -48,6 +51,13 @@ int main() {
       int ntx, nty, nkc;
       em_tiles(g, prec, 1, &ntx, &nty, &nkc);
       std::printf("%d %d %d\n", ntx, nty, nkc);
+    } else if (std::string(what) == "chunk") {
+      const int n = 200;
+      volatile int kc = 0;
+      const auto t0 = std::chrono::steady_clock::now();
+      for (int q = 0; q < n; ++q) kc = prec == ETM_PREC_FP64 ? mech::cell_kchunk<double>(g) : mech::cell_kchunk<float>(g);
+      const auto ns = std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - t0);
+      std::printf("%d %lld\n", int(kc), (long long)ns.count() / n);
     } else {
       std::printf("error unknown query\n");
     }

@@ -70,3 +70,31 @@ def test_mixed_form_switches_where_a_step_streams(ask):
         assert (tx, ty) == want and kc == nz + 1, (nx, ny, nz, tx, ty)
         forms.append(tiles)
     assert forms[:3] == [False, True, True] and not forms[6] and forms[7]
+
+
+def hex8_chunk(nx, ny, nz, resident):
+    """Fewest generations of resident blocks times planes per block, the longest chunk on a tie."""
+    tiles = -(-(nx + 1) // 31) * -(-(ny + 1) // 7)
+    rows = max(1024, -(-(nx + 1) // 64) * -(-(ny + 1) // 4) * (nz + 1))
+    best, least = nz + 1, None
+    for kc in range(nz + 1, 1, -1):
+        blocks = tiles * -(-(nz + 1) // kc)
+        if blocks > rows and kc <= nz:
+            break
+        cost = -(-blocks // resident) * (kc + 2)
+        if least is None or cost < least:
+            best, least = kc, cost
+    return best
+
+
+# The chunk of the HEX8 operator is chosen at every launch of a solve, about ten
+# times per iteration: tall meshes must not pay for a search over all their
+# planes (0.4 ms and more for 60,000; a launch's own cost is a few microseconds).
+@pytest.mark.parametrize("precision,resident", [(etm.ETM_PREC_FP64, 512), (etm.ETM_PREC_MIXED, 1024)])
+def test_hex8_chunk_is_the_best_and_quick_to_choose(ask, precision, resident):
+    shapes = [(1, 1, 1), (3, 3, 1), (30, 6, 2), (31, 7, 5), (97, 83, 33), (160, 152, 48), (256, 256, 64), (512, 512, 64),
+              (1024, 1024, 128), (300, 300, 3), (32800, 7, 1), (8, 8, 499), (40, 36, 400), (31, 7, 6000), (7, 7, 20000),
+              (1, 1, 60000)]
+    for shape, (kc, ns) in zip(shapes, ask(["chunk %d %d %d %d" % (precision, *s) for s in shapes])):
+        assert kc == hex8_chunk(*shape, resident), (shape, kc)
+        assert ns < 100000, (shape, ns)
